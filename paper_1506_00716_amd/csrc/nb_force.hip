@@ -149,6 +149,11 @@ __device__ __forceinline__ float lane_read(float v, int k)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
 }
 
+// What a force sum over x starts from: +0, or NaN for a coordinate that is not
+// finite.  No pair of such an atom is within r_cut, so nothing else would carry it to
+// the gather, which reports it.  (An FMA in the place of the move.)
+__device__ __forceinline__ float zero_of(float x) { return __builtin_fmaf(0.0f, x, 0.0f); }
+
 // What the pair arithmetic leaves for the energies
 struct Pair {
     float rinv, rinv6, c6, c12, w;  // (c6, c12 with LJ == 1; w, kt with COUL == 2)
@@ -238,7 +243,7 @@ __device__ __forceinline__ int item_system(const int* item_prefix, int n_sys, in
 // the same.
 //
 // WAVES: waves per SIMD that the registers leave room for (1: as it comes).  The
-// plain Ewald pass takes 100 registers, 4 waves, and 96 for 5: better for a launch of
+// plain Ewald pass takes 99 registers, 4 waves, and 96 for 5: better for a launch of
 // more items than 4 waves per SIMD take at once (200,003 atoms 118.0 us against
 // 126.4), not for one that they take (24,389 atoms, 3,890 items, 24.6 against 24.1).
 // The Ewald tables are loaded in a branch of their own with the item, so that their
@@ -394,7 +399,11 @@ __global__ __launch_bounds__(256, WAVES) void k_force8(const SysDev* __restrict_
         }
         float fix[G], fiy[G], fiz[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) fix[g] = fiy[g] = fiz[g] = 0.0f;
+        for (int g = 0; g < G; ++g) {
+            fix[g] = zero_of(xi[g].x);
+            fiy[g] = zero_of(xi[g].y);
+            fiz[g] = zero_of(xi[g].z);
+        }
         float elj = 0.f, ec = 0.f, wxx = 0.f, wyy = 0.f, wzz = 0.f, wxy = 0.f, wxz = 0.f, wyz = 0.f;
 
         // the previous entry's j-partial, stored one entry late: after the wait
@@ -451,7 +460,7 @@ __global__ __launch_bounds__(256, WAVES) void k_force8(const SysDev* __restrict_
             if (LJ == 1) ljj_n = gld2(ljs + (size_t)cj_n * M, boff / 2);
             const unsigned int im = (meta >> (PRUNE ? kMetaOuter : kMetaInner)) & 255u;
             unsigned int pin_m = 0u;  // (pruning) i-clusters with a pair within r_inner
-            float fjx = 0.f, fjy = 0.f, fjz = 0.f;
+            float fjx = zero_of(xj.x), fjy = zero_of(xj.y), fjz = zero_of(xj.z);
             // the i-cluster that is the entry's j-cluster (none if not in 0..7)
             const int gs = cj - gi * G;
             const unsigned long long selfm = (meta & 255u) == (unsigned int)kShiftZero ? once : offd;
@@ -673,7 +682,7 @@ __global__ __launch_bounds__(256, 4) void k_force8_split(const SysDev* __restric
             xj_n = gld4(xq + (size_t)lane_read(enl.x, k) * M, boff);
             if (LJ == 1) ljj_n = gld2(ljs + (size_t)lane_read(enl.x, k) * M, boff / 2);
             const unsigned int im = (meta >> kMetaInner) & 255u;
-            float fjx = 0.f, fjy = 0.f, fjz = 0.f;
+            float fjx = zero_of(xj.x), fjy = zero_of(xj.y), fjz = zero_of(xj.z);
             const int gs = cj - gi * G;
             const unsigned long long selfm = (meta & 255u) == (unsigned int)kShiftZero ? once : offd;
 #pragma unroll
@@ -706,7 +715,7 @@ __global__ __launch_bounds__(256, 4) void k_force8_split(const SysDev* __restric
             const float4 x = gld4(xq + (size_t)gi * (G * M), aoff + (unsigned int)g * (M * sizeof(float4)));
             const int from = slot + __popc(iml & ((1 << g) - 1));
             unsigned long long on = __builtin_amdgcn_ballot_w64(((iml >> g) & 1) != 0);
-            float fx = 0.f, fy = 0.f, fz = 0.f;
+            float fx = zero_of(x.x), fy = zero_of(x.y), fz = zero_of(x.z);
             // (read an entry ahead)
             const auto read = [&](int e, float& f, float4& xj) {
                 f = fsl[min(lane_read(from, e), kSplitPairs - 1)][lane];
