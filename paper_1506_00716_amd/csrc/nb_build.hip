@@ -203,12 +203,12 @@ __global__ __launch_bounds__(256) void k_build_clear(const SysDev* __restrict__ 
     }
     if (i < d.max_groups * d.G) gst(&d.jfill[i], 0);
     // displacement partials: blocks [0, sys_blocks) stride over the atoms (the
-    // same decomposition alone and in a batch); the other partial slots are 0
-    const int nb = sys_blocks(d.n_atoms);
-    if ((int)blockIdx.x >= nb) {
-        if ((int)blockIdx.x < kKeBlocks && threadIdx.x == 0) d.disp[blockIdx.x] = 0.0;
-        return;
-    }
+    // same decomposition alone and in a batch); the others that the column scan
+    // reads are 0 (the gather before a rebuild leaves more of them than this grid
+    // has blocks)
+    const int nb = sys_blocks(d.n_atoms), np = guard_partials(d);
+    for (int k = nb + i; k < np; k += gridDim.x * blockDim.x) gst(&d.disp[k], 0.0);
+    if ((int)blockIdx.x >= nb) return;
     __shared__ double sh[256];
     double m = 0.0;
     for (int a = blockIdx.x * blockDim.x + threadIdx.x; a < d.n_atoms; a += nb * blockDim.x) {
@@ -313,7 +313,7 @@ __device__ __forceinline__ void col_scan(const SysDev& d, int mode)
         // the buffer (the only way a pair could enter r_cut unlisted)
         __shared__ double shd[NT];
         double m = 0.0;
-        const int np = min(kKeBlocks, (d.max_groups * kGroup + 3) / 4);  // (a partial per 4 clusters at most)
+        const int np = guard_partials(d);
         for (int k = threadIdx.x; k < np; k += blockDim.x) {
             const double u = gld(&d.disp[k]);
             m = (u > m || u != u) ? u : m;

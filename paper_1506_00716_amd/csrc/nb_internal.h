@@ -268,6 +268,15 @@ struct SysDev {
     const double* pme_e;  // [8] reciprocal + self + background energy, Xi xx,yy,zz,xy,xz,yz
 };
 
+// The list-buffer guard's partials: every kernel that measures a list lifetime leaves
+// this many (a gather's blocks have 4 clusters each, or more; an atom loop has fewer
+// blocks), zero where it has nothing, and the column scan reads them all
+__host__ __device__ inline int guard_partials(const SysDev& d)
+{
+    const int n = d.max_groups * (kGroup / 4);
+    return n > kKeBlocks ? kKeBlocks : n;
+}
+
 // Smooth particle-mesh Ewald of one system: a K0 x K1 x K2 grid along the
 // lattice vectors a, b, c, cardinal B-splines of order `order`.
 struct PmeDev {

@@ -341,8 +341,7 @@ __global__ __launch_bounds__(256) void k_gather(const SysDev* __restrict__ table
         if (t < ST_COUNT && t != ST_SATURATE && t != ST_BADPOS) gst(&d.status[t], 0);
         // guard partials past this grid
         if (bx == 0)
-            for (int k = gridDim.x + threadIdx.x; k < min(kKeBlocks, d.max_groups * (kGroup / 4)); k += blockDim.x)
-                gst(&d.disp[k], 0.0);
+            for (int k = gridDim.x + threadIdx.x; k < guard_partials(d); k += blockDim.x) gst(&d.disp[k], 0.0);
     }
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
