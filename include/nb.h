@@ -244,7 +244,7 @@ nb_status nb_pme_forces(nb_sys *sys, const double *x_dev, float *f_dev, double *
  * NULL) the count.  Synchronises at the end.
  * Errors: if a rebuild inside the call needs more list capacity than the arena
  * holds (with build checks on, the default), the call returns NB_ERR_CAPACITY
- * with x, v and the step counter at the last completed step, the energy rows of
+ * with x, v, f and the step counter at the last completed step, the energy rows of
  * the completed steps in ener_trace_host / *n_rows, and nb_sys_needed_bytes set:
  * grow the arena (nb_sys_set_arena) and call again for the remaining steps. */
 nb_status md_step(nb_sys *sys, double *x_dev, double *v_dev, float *f_dev, double dt_ps,
@@ -372,9 +372,11 @@ nb_status nb_sys_get_timings(nb_sys *sys, double out[6]);
  * displacement within one interval, out[3] = intervals in which it reached
  * (r_inner - r_cut)/2 (0 and 0 without pruning).  Synchronises. */
 nb_status nb_sys_buffer_stats(nb_sys *sys, double out[4]);
-/* md_step checks list capacity after every rebuild by default (one host
- * synchronisation per rebuild); off defers the check to the end of the call
- * (a capacity overflow then fails the call after the fact). */
+/* md_step checks list capacity after every rebuild by default: the host looks at
+ * the build's verdict some steps later, without waiting for the stream, at the
+ * latest before the next rebuild's step (with dynamic pruning it synchronises once
+ * per rebuild).  Off defers the check to the end of the call (a capacity overflow
+ * then fails the call after the fact). */
 nb_status nb_sys_set_build_checks(nb_sys *sys, int32_t on);
 
 /* ------------------------------------------------------------------------ */

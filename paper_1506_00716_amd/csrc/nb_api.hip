@@ -1339,7 +1339,8 @@ nb_status md_step(nb_sys* s, double* x_dev, double* v_dev, float* f_dev, double 
     // A rebuild's capacity is looked at late: its verdict comes in a pinned word
     // while the steps after it are already enqueued, and is waited for before the
     // gather that overwrites x_bak, v_bak (the state to go back to), before the rows
-    // are flushed and at the end.  (Waiting after each rebuild left the GPU idle for
+    // are flushed and at the end.  The gathers of those steps leave x, v and f alone if
+    // the list did not fit.  (Waiting after each rebuild left the GPU idle for
     // about 15 us.)  With dynamic pruning the wait stays after the rebuild: the
     // steps enqueued meanwhile would add to the prune statistics.
     const bool late_check = s->check_builds && !s->h.prune_on;
@@ -1479,7 +1480,7 @@ nb_status md_step(nb_sys* s, double* x_dev, double* v_dev, float* f_dev, double 
             r = late_verdict();
             if (r) return r;
         }
-        HIPCHK(s->ctx, launch_gather_kick(s->d_desc, 1, s->bounds, dt_ps, ener, st, next));
+        HIPCHK(s->ctx, launch_gather_kick(s->d_desc, 1, s->bounds, dt_ps, ener, st, next, false, late_check));
         moved = next > 0;
         if (ener) {
             // the energy row: by an extra block of the next step's pair kernel

@@ -1445,6 +1445,7 @@ __global__ __launch_bounds__(1024) void k_list_scan(const SysDev* __restrict__ t
     const SysDev& d = table[blockIdx.x];
     __shared__ int smem[40];
     const int ng = gld(&d.n_groups[0]);
+    const int over0 = gld(&d.status[ST_OVERFLOW]);  // (groups or candidates, by the kernels before)
     if (blockIdx.y > 0) {
         // (8 clusters per thread, one group's: 32 bytes)
         const int ncl = ng * d.G, first = ((int)blockIdx.y - 1) * kScanSlice, c = first + 8 * (int)threadIdx.x;
@@ -1529,17 +1530,16 @@ __global__ __launch_bounds__(1024) void k_list_scan(const SysDev* __restrict__ t
             d.status[ST_OVERFLOW] = 1;
             atomicMax(&d.status[ST_NEED_ITEM], ni);
         }
-        const bool over = ne > d.ent_cap || ni > d.item_cap;
-        d.n_ent[0] = over ? 0 : ne;
+        const bool over = ne > d.ent_cap || ni > d.item_cap, any = over || over0 != 0;
+        d.n_ent[0] = over ? ~0 : any ? ~ne : ne;
         d.n_items[0] = over ? 0 : ni;
         if (item_prefix) {
             item_prefix[0] = 0;
             item_prefix[1] = over ? 0 : ni;
         }
         if (seen)
-            __hip_atomic_store(seen,
-                               ((unsigned long long)(over || gld(&d.status[ST_OVERFLOW]) != 0 ? 1 : 0) << 32) | seq,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(seen, ((unsigned long long)(any ? 1 : 0) << 32) | seq, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -1591,7 +1591,7 @@ __global__ __launch_bounds__(256) void k_list_write(const SysDev* __restrict__ t
     int2 cd = gld(&cand[min((int)threadIdx.x, cap - 1)]);
     __shared__ int tot[2][4];
     if (gi >= ng) return;
-    if (ne == 0) return;  // empty list, or overflow: list unusable
+    if (ne == 0 || ne == ~0) return;  // empty list, or overflow: list unusable
     const int ncand = min(nc, cap);
     const int nit = it1 - it0;
     // the group's weight wg is cut into its nit = ceil(wg / W) items at the

@@ -245,7 +245,7 @@ struct SysDev {
     int* jstart;          // [max_groups*G+1] entries that list each cluster as j (CSR)
     int* jfill;           // [max_groups*G] their counts, counted down as the list is written
     int* n_items;         // [1]
-    int* n_ent;           // [1]
+    int* n_ent;           // [1] entries written; ~ of it if a capacity was exceeded
     // ---- reductions and outputs -----------------------------------------
     double* ke_part;      // [kKeBlocks]
     double* eout;         // [16]: E_lj, E_c, Xi xx,yy,zz,xy,xz,yz, KE; kEoutAt bytes after status
@@ -428,9 +428,10 @@ hipError_t launch_kick_drift_stage(const SysDev* table, int n_sys, const Bounds&
 // next: 0 = gather + half-kick; 1 = and the next step's half-kick + drift, and
 // the list build's clears and buffer-guard partials (a rebuild follows);
 // 2 = and also the staging of the new positions (no list rebuild due).
-// open: the first positions of a run (no half-kick closes a step; next 1 or 2)
+// open: the first positions of a run (no half-kick closes a step; next 1 or 2);
+// held: nothing moves and no force is stored if the list ran out of capacity
 hipError_t launch_gather_kick(const SysDev* table, int n_sys, const Bounds& b, double dt, bool ke, hipStream_t s,
-                              int next = 0, bool open = false);
+                              int next = 0, bool open = false, bool held = false);
 hipError_t launch_export_count(const SysDev* table, const Bounds& b, hipStream_t s);
 hipError_t launch_export_write(const SysDev* table, const Bounds& b, int* pairs_dev,
                                long long cap, hipStream_t s);

@@ -285,7 +285,9 @@ __device__ inline int cluster_blocks(int n_clusters)
 // last build per block, x recorded for the next one); 2 = half-kick, drift and
 // the staging of the new x (as k_kick_drift_stage).  open: the forces of a run's
 // first positions, with no step to close: only the next step's half-kick and drift
-// (NEXT 1 or 2).
+// (NEXT 1 or 2).  held: a list that ran out of capacity moves nothing, x, v and f
+// stay as they are (the host has enqueued past a rebuild whose verdict it does not
+// know yet; see md_step).
 // FMAX (without KICK): also the largest |F|^2 per block into fmax_part (NaN wins)
 // WIDE (all systems of 8-atom clusters): R = 2
 // ENER (one system, without KICK): block 0 forms the energy row from the pair
@@ -298,7 +300,7 @@ __device__ inline int cluster_blocks(int n_clusters)
 // the launch is about 2.5).
 template <bool KICK, bool FMAX, int NEXT, bool WIDE, bool ENER = false>
 __global__ __launch_bounds__(256) void k_gather(const SysDev* __restrict__ table, double dt, int ke, int open,
-                                                const int* flags, int ener_row, double ener_step)
+                                                int held, const int* flags, int ener_row, double ener_step)
 {
     if (flags && !flags[blockIdx.y]) return;  // (only the force-only gather takes flags)
     const SysDev& d = table[blockIdx.y];
@@ -373,7 +375,9 @@ __global__ __launch_bounds__(256) void k_gather(const SysDev* __restrict__ table
     // partial rows written by the force kernel: a list whose build ran out of
     // capacity has none (its offsets may point past the partial arrays, so the
     // row ranges below are clamped to what exists)
-    const int n_it = gld(n_items_p), n_en = gld(n_ent_p);
+    const int n_it = gld(n_items_p), ent_w = gld(n_ent_p);
+    const bool over = ent_w < 0;
+    const int n_en = over ? ~ent_w : ent_w;
     const int n_cl = __builtin_amdgcn_readfirstlane(gld(n_groups_p)) * kGroup;
     const int nb = cluster_blocks(n_cl);           // kinetic-energy partials
     const int stride = nb * 4 * M;                 // slots per pass of all waves
@@ -388,6 +392,7 @@ __global__ __launch_bounds__(256) void k_gather(const SysDev* __restrict__ table
         if (FMAX && threadIdx.x == 0) gst(&d.fmax_part[bx], 0.0);
         return;
     }
+    if (KICK && over && held) return;
     bool bad = false;
     double kin = 0.0;
     // the largest squared displacement since the last build (NEXT 1) or squared
@@ -610,13 +615,13 @@ static int gather_blocks(const Bounds& b)
 }
 
 template <bool KICK, bool FMAX, int NEXT, bool ENER = false>
-static void launch_gather(const SysDev* table, int n_sys, const Bounds& b, double dt, bool ke, bool open,
+static void launch_gather(const SysDev* table, int n_sys, const Bounds& b, double dt, bool ke, bool open, bool held,
                           const int* flags, hipStream_t s, int ener_row = -1, double ener_step = 0.0)
 {
     hipLaunchKernelGGL((gather_wide(b) ? k_gather<KICK, FMAX, NEXT, true, ENER>
                                        : k_gather<KICK, FMAX, NEXT, false, ENER>),
                        dim3(gather_blocks(b) + (ENER ? 1 : 0), n_sys), dim3(256), 0, s, table, dt, ke ? 1 : 0,
-                       open ? 1 : 0, flags, ener_row, ener_step);
+                       open ? 1 : 0, held ? 1 : 0, flags, ener_row, ener_step);
 }
 
 hipError_t launch_finalize(const SysDev* table, int n_sys, const Bounds& b, bool fp32, hipStream_t s,
@@ -624,9 +629,9 @@ hipError_t launch_finalize(const SysDev* table, int n_sys, const Bounds& b, bool
 {
     (void)fp32;
     if (ener)
-        launch_gather<false, false, 0, true>(table, n_sys, b, 0.0, false, false, flags, s, trace_row, step_value);
+        launch_gather<false, false, 0, true>(table, n_sys, b, 0.0, false, false, false, flags, s, trace_row, step_value);
     else
-        launch_gather<false, false, 0>(table, n_sys, b, 0.0, false, false, flags, s);
+        launch_gather<false, false, 0>(table, n_sys, b, 0.0, false, false, false, flags, s);
     return hipGetLastError();
 }
 
@@ -674,14 +679,14 @@ hipError_t launch_kick_drift_stage(const SysDev* table, int n_sys, const Bounds&
 }
 
 hipError_t launch_gather_kick(const SysDev* table, int n_sys, const Bounds& b, double dt, bool ke, hipStream_t s,
-                              int next, bool open)
+                              int next, bool open, bool held)
 {
     if (next == 2)
-        launch_gather<true, false, 2>(table, n_sys, b, dt, ke, open, nullptr, s);
+        launch_gather<true, false, 2>(table, n_sys, b, dt, ke, open, held, nullptr, s);
     else if (next == 1)
-        launch_gather<true, false, 1>(table, n_sys, b, dt, ke, open, nullptr, s);
+        launch_gather<true, false, 1>(table, n_sys, b, dt, ke, open, held, nullptr, s);
     else
-        launch_gather<true, false, 0>(table, n_sys, b, dt, ke, open, nullptr, s);
+        launch_gather<true, false, 0>(table, n_sys, b, dt, ke, open, held, nullptr, s);
     return hipGetLastError();
 }
 
@@ -704,7 +709,7 @@ int prune_guard_arg(int n_atoms, int cur, int fold)
 
 hipError_t launch_gather_fmax(const SysDev* table, const Bounds& b, hipStream_t s)
 {
-    launch_gather<false, true, 0>(table, 1, b, 0.0, false, false, nullptr, s);
+    launch_gather<false, true, 0>(table, 1, b, 0.0, false, false, false, nullptr, s);
     return hipGetLastError();
 }
 
