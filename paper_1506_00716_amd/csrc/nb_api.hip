@@ -813,6 +813,7 @@ nb_status nbh::do_build(nb_sys* s, bool exact)
     int stv[ST_COUNT];
     nb_status r = read_status(s, stv);
     if (r) return r;
+    s->items_built = stv[ST_ITEMS];
     if (stv[ST_OVERFLOW]) return capacity_error(s, stv);
     s->list_valid = true;
     // a list built afresh starts the dynamic-prune schedule and its guard here
@@ -830,12 +831,12 @@ nb_status nbh::need_mailbox(nb_sys* s)
     return NB_OK;
 }
 
-// launch_force's few_items of one system, from its mean density
 int nbh::few_items(const nb_sys* s)
 {
     const nb_params& p = s->p;
     return split_items(s->M, s->jtile, (double)p.n_atoms * p.n_atoms / (p.box[0] * p.box[1] * p.box[2]) * p.r_list *
-                                           p.r_list * p.r_list);
+                                           p.r_list * p.r_list,
+                       s->items_built);
 }
 
 // the pair kernel at the staged positions (beside the reciprocal part, if any),
@@ -1387,7 +1388,8 @@ nb_status md_step(nb_sys* s, double* x_dev, double* v_dev, float* f_dev, double 
                     return fail(s->ctx, NB_ERR_DEVICE, "a list build did not report");
             }
         }
-        if (!(w >> 32)) return NB_OK;
+        s->items_built = (int)(w >> 32 & 0x7fffffffull);
+        if (!(w >> 63)) return NB_OK;
         int stv[ST_COUNT];
         nb_status q = read_status(s, stv);
         if (q) return q;
@@ -1440,6 +1442,7 @@ nb_status md_step(nb_sys* s, double* x_dev, double* v_dev, float* f_dev, double 
                 int stv[ST_COUNT];
                 r = read_status(s, stv);
                 if (r) return r;
+                s->items_built = stv[ST_ITEMS];
                 if (stv[ST_OVERFLOW]) {
                     s->step -= 1;
                     return undo_rebuild(stv);

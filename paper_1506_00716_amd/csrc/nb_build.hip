@@ -1435,7 +1435,7 @@ __global__ __launch_bounds__(256) void k_count_kept(const SysDev* __restrict__ t
 //    million atoms, latency over latency; 16.8
 //    now (24000 atoms: 7.3 and 4.8).  item_prefix (one system
 //    only): the prefix {0, items} the force kernel reads; seen (one system, may be
-//    NULL): the build's verdict for the host {seq, capacity exceeded}.
+//    NULL): the build's verdict for the host {seq, items, capacity exceeded}.
 constexpr int kScanSlice = 8 * 1024;
 
 __global__ __launch_bounds__(1024) void k_list_scan(const SysDev* __restrict__ table, const int* flags,
@@ -1537,9 +1537,10 @@ __global__ __launch_bounds__(1024) void k_list_scan(const SysDev* __restrict__ t
             item_prefix[0] = 0;
             item_prefix[1] = over ? 0 : ni;
         }
+        d.status[ST_ITEMS] = ni;
         if (seen)
-            __hip_atomic_store(seen, ((unsigned long long)(any ? 1 : 0) << 32) | seq, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(seen, (any ? 1ull << 63 : 0ull) | (unsigned long long)(unsigned int)ni << 32 | seq,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

@@ -30,6 +30,8 @@ __global__ void k_ens_energy(const SysDev* __restrict__ table, int n, double* ou
 
 size_t al(size_t v) { return (v + 255) & ~size_t(255); }
 
+constexpr int kStatusWords = 64;  // (256 bytes: the prefixes follow without a gap)
+
 struct EnsClass {
     int M, coul, lj, fp32;
     int off, cnt;
@@ -57,6 +59,7 @@ struct nb_ens {
     std::vector<SysDev> h_table;
     std::vector<EnsClass> classes;
     std::vector<int> h_eflags;  // host copy of d_eflags (kept until the upload has run)
+    std::vector<int> h_status;  // host copy of d_status and, after a build, the item prefixes
     Bounds bounds;
     bool dirty;
     hipStream_t cap_stream;
@@ -78,11 +81,11 @@ size_t ens_layout(int max_systems, char* base, nb_ens* e)
         return p;
     };
     char* t = take(sizeof(SysDev) * (size_t)max_systems);
+    char* s = take(sizeof(int) * kStatusWords);  // (in front of the prefixes: one copy returns both)
     char* p = take(sizeof(int) * (size_t)(2 * max_systems + 64));
     char* p2 = take(sizeof(int) * (size_t)(2 * max_systems + 64));
     char* f = take(sizeof(int) * (size_t)max_systems);
     char* ef = take(sizeof(int) * (size_t)max_systems);
-    char* s = take(sizeof(int) * 4);
     char* en = take(sizeof(double) * 3 * (size_t)max_systems);
     if (e) {
         e->d_table = (SysDev*)t;
@@ -190,17 +193,19 @@ nb_status ens_prefixes(nb_ens* e, hipStream_t st, int* prefix = nullptr, const i
 // faults: also report saturated / non-finite members (end of a call); a
 // rebuild inside the call checks capacity only, so every member still takes
 // all the steps of the call and a failing one can be isolated afterwards.
-// over (may be NULL): per member, whether its list ran out of capacity (each
-// such member gets its needed arena size and loses its list)
+// over (after a build; may be NULL): per member, whether its list ran out of capacity
+// (each such member gets its needed arena size and loses its list)
 nb_status ens_check(nb_ens* e, bool faults, std::vector<char>* over = nullptr)
 {
-    int st[2];
     hipStream_t s = e->ctx->stream;
     const int n = (int)e->members.size();
     if (over) over->assign(n, 0);
     HIPCHK(e->ctx, launch_ens_status(e->d_table, n, e->d_status, s));
-    HIPCHK(e->ctx, hipMemcpyAsync(st, e->d_status, sizeof(st), hipMemcpyDeviceToHost, s));
+    e->h_status.resize(over ? kStatusWords + n + e->classes.size() : 2);
+    HIPCHK(e->ctx, hipMemcpyAsync(e->h_status.data(), e->d_status, sizeof(int) * e->h_status.size(),
+                                  hipMemcpyDeviceToHost, s));
     HIPCHK(e->ctx, hipStreamSynchronize(s));
+    const int* st = e->h_status.data();
     if (st[0]) {
         // the members that overflowed, with their needed sizes
         std::string who;
@@ -217,6 +222,19 @@ nb_status ens_check(nb_ens* e, bool faults, std::vector<char>* over = nullptr)
         }
         return nbh::fail(e->ctx, NB_ERR_CAPACITY, "ensemble member pair-list capacity exceeded: " + who);
     }
+    if (over)
+        // the items of these lists, for the choice of the pair kernel's form
+        for (EnsClass& c : e->classes) {
+            const int form = force_form(c.few);
+            const int* pre = st + kStatusWords + c.prefix_off;
+            c.few = 0;
+            for (int k = 0; k < c.cnt; ++k) {
+                nb_sys* m = e->members[c.off + k];
+                m->items_built = pre[k + 1] - pre[k];
+                c.few = std::min(c.few + nbh::few_items(m), kSplitNever);
+            }
+            if (force_form(c.few) != form) drop_graph(e);
+        }
     if (faults && st[1])
         return nbh::fail(e->ctx, NB_ERR_NONFINITE, "non-finite position or force beyond the fixed-point range in an ensemble member");
     return NB_OK;

@@ -1168,12 +1168,6 @@ static ForceFn pick_m(int coul, int lj, bool ener, bool prune)
     }
 }
 
-// Items (as split_items counts them, a few per cent too many) past which 4 waves per
-// SIMD on 256 CUs, 4096, do not take all at once: 26,000 atoms (4,190) 31.7 us a call
-// with 4 waves and 32.2 with 5, 28,000 (4,510) 37.1 and 34.8, 30,000 38.7 and 35.5,
-// 50,000 49.4 and 48.3, 80,000 66.6 and 63.5.
-constexpr int kManyItems = 4400;
-
 static ForceFn pick_split(int coul, int lj)
 {
     switch (coul * 2 + lj) {
@@ -1186,10 +1180,10 @@ static ForceFn pick_split(int coul, int lj)
     }
 }
 
-int split_items(int M, int jtile, double n_rho_r3)
+int split_items(int M, int jtile, double n_rho_r3, int built)
 {
     if (M != 8 || item_weight(M, jtile) > kSplitWeight) return kSplitNever;
-    return (int)std::min(0.31 * n_rho_r3 / item_weight(M, jtile), (double)kSplitNever);
+    return (int)std::min(std::max(0.31 * n_rho_r3 / item_weight(M, jtile), (double)built), (double)kSplitNever);
 }
 
 hipError_t launch_force(const SysDev* table, int n_sys, const int* item_prefix, int M, int coulomb,
@@ -1206,9 +1200,10 @@ hipError_t launch_force(const SysDev* table, int n_sys, const int* item_prefix, 
     // than the CUs hold at once: on the 1M-atom slab one resident round of
     // blocks (1024) is 4 % slower.  max_blocks > 0 caps it (a multiple of 8 so
     // the XCD-aware block remap in the kernel is a bijection)
-    const bool split = M == 8 && !ener && !prune && few_items <= kSplitItems;
+    const int form = force_form(few_items);
+    const bool split = M == 8 && !ener && !prune && form == 0;
     if (split) fn = pick_split(coulomb, lj);
-    else if (M == 8 && coulomb == 2 && lj == 0 && !ener && !prune && few_items > kManyItems)
+    else if (M == 8 && coulomb == 2 && lj == 0 && !ener && !prune && form == 2)
         fn = k_force8<2, 0, false, false, 5>;
     int blocks = split ? total_item_cap : (total_item_cap + 3) / 4;
     if (blocks > 4096) blocks = 4096;

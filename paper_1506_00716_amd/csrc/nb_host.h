@@ -63,6 +63,7 @@ struct nb_sys {
     // one synchronisation
     void* mailbox = nullptr;
     unsigned int build_seq = 0;  // rebuilds whose verdict was asked for
+    int items_built = 0;         // work items of the last build that the host has heard of
     // per-phase HIP-event timers (md_step): pairs of events around each launch
     bool timing;
     int timing_every;     // mark one of every timing_every force launches / rebuilds
@@ -133,7 +134,7 @@ nb_status status_result(nb_sys* s, const int st[nbi::ST_COUNT]);
 //    evaluations, where the PME chain is the longer)
 nb_status pme_fork(nb_sys* s, const double* x, bool ener);
 nb_status pme_join(nb_sys* s);
-int few_items(const nb_sys* s);
+int few_items(const nb_sys* s);  // launch_force's, of one system
 nb_status pair_beside_pme(nb_sys* s, const double* x, bool ener, bool prune, int guard = -1);
 // the pair kernel's grid beside the PME kernels: 4 blocks of 4 waves per CU.  At 100
 // registers they leave a SIMD 96 more, a slot for the PME kernels' waves (24,389 atoms

@@ -145,7 +145,7 @@ __device__ inline int sys_blocks(int n_atoms)
 
 // status word indices
 enum { ST_OVERFLOW = 0, ST_NEED_CAND = 1, ST_NEED_ENT = 2, ST_NEED_ITEM = 3, ST_NEED_GROUPS = 4,
-       ST_SATURATE = 5, ST_BIGCOL = 6, ST_BADPOS = 7, ST_COUNT = 8 };
+       ST_SATURATE = 5, ST_BIGCOL = 6, ST_BADPOS = 7, ST_ITEMS = 8, ST_COUNT = 9 };  // ST_ITEMS: work items of the build
 
 struct SysDev {
     // ---- what the pair kernel reads for every work item, in four cache lines --
@@ -371,8 +371,8 @@ struct Bounds {
 // rebuild, 2 = first build (x only recorded); without flags, first says which.
 // cleared: the gather before it already cleared the counters and status words
 // and took the list-buffer guard's partials (md_step's rebuilds).  seen (one
-// system): a word in pinned host memory that receives {seq, 1 if a capacity was
-// exceeded} when that is known
+// system): a word in pinned host memory that receives {seq, work items | 1 << 31 if a
+// capacity was exceeded} when that is known
 hipError_t launch_build(const SysDev* table, int n_sys, const Bounds& b, const int* flags, hipStream_t s,
                         bool exact, int status_clear = 0, int* item_prefix = nullptr, bool first = false,
                         bool cleared = false, unsigned long long* seen = nullptr, unsigned int seq = 0);
@@ -391,6 +391,13 @@ hipError_t launch_state_copy(const SysDev* table, int n_sys, const Bounds& b, in
 // against 22, of 8,500 with reaction field (1,030 items) 18.8 against 21.6; of 10,000
 // (1,210) 20.5 against 19.5, of 8,500 with Ewald (1,370) 23.4 against 23.1.
 constexpr int kSplitItems = 1150, kSplitNever = 1 << 24;
+// Items past which 4 waves per SIMD on 256 CUs, 4096, do not take all at once (a uniform
+// liquid's are counted a few per cent too high): 26,000 atoms (4,190) 31.7 us a call
+// with 4 waves and 32.2 with 5, 28,000 (4,510) 37.1 and 34.8, 30,000 38.7 and 35.5,
+// 50,000 49.4 and 48.3, 80,000 66.6 and 63.5.
+constexpr int kManyItems = 4400;
+// which of the forms above a plain launch of that many items takes
+inline int force_form(int few_items) { return few_items <= kSplitItems ? 0 : few_items > kManyItems ? 2 : 1; }
 // prune: the force pass also prunes every entry's i-cluster mask to r_inner
 // (from the build's mask), and later passes evaluate the pruned mask.
 // max_blocks > 0 caps the persistent grid (its waves loop over the work items).
@@ -402,8 +409,12 @@ hipError_t launch_force(const SysDev* table, int n_sys, const int* item_prefix, 
                         int lj, bool ener, int max_blocks, int total_item_cap, hipStream_t s, bool prune = false,
                         int red_row = -1, double red_step = 0.0, int few_items = kSplitNever);
 // few_items: about the items of the launch, split_items summed over its systems; up
-// to kSplitItems of them are worked on by a block each
-int split_items(int M, int jtile, double n_rho_r3);
+// to kSplitItems of them are worked on by a block each.  built: the items of the last
+// build that the host has heard of (0: none).  The estimate from the mean density
+// stands where it is higher: it is what the lines above were measured with, and holds
+// where no build has run; a droplet's items are many times as many (24,389 atoms in a
+// box of 4 times their edge, Ewald: 6,490 items, 49.6 us a call and 63.9 by the estimate)
+int split_items(int M, int jtile, double n_rho_r3, int built);
 // dynamic-prune guard of one system: check = 1: the largest displacement since
 // x_prune into partial buffer cur; then x_prune = x.  fold: first fold the
 // previous interval's partials (buffer 1 - cur) into the statistics
