@@ -259,13 +259,20 @@ nb_status ens_step_end(nb_ens* e, hipStream_t st, double dt, bool ener, int next
 // Most plain steps in one replayed graph.  The GPU idles for about 8 us before
 // each replay, so a graph holds a run of steps: 20 steps of 5 systems of 2000 to
 // 8000 atoms take 785 us (843 with a graph per step, 783 with plain launches), 50
-// steps of 2 systems of 1000 to 2000 atoms 1397 (1541, 1383).
+// steps of 2 systems of 1000 to 2000 atoms 1397 (1541, 1383).  The graph kept is that
+// of the longest run met so far: a shorter run is launched plainly, a longer one is
+// captured anew (at most kGraphSteps - 2 times), so that a short first call does not
+// leave its short graph to all later ones.
 constexpr int kGraphSteps = 16;
 
 // Capture n_plain plain steps on a private stream, for replay on the context stream
 nb_status capture_steps(nb_ens* e, double dt, int n_plain)
 {
-    drop_graph(e);
+    if (e->graph_ok) {
+        // (a replay of it may still run)
+        HIPCHK(e->ctx, hipStreamSynchronize(e->ctx->stream));
+        drop_graph(e);
+    }
     HIPCHK(e->ctx, hipStreamBeginCapture(e->cap_stream, hipStreamCaptureModeThreadLocal));
     nb_status rc = NB_OK;
     for (int k = 0; k < n_plain && !rc; ++k) rc = ens_step_end(e, e->cap_stream, dt, false, 2);
@@ -483,7 +490,7 @@ nb_status nb_ens_step(nb_ens* e, int32_t n_steps, double dt, int32_t nstlist, in
             // plain steps from here whose gather goes on to a plain step
             int run = 0;
             while (run < kGraphSteps && k + run + 1 < n_steps && due(run + 1) == 0 && due(run + 2) == 0) ++run;
-            if (run >= 2 && (!e->graph_ok || e->graph_dt != dt)) {
+            if (run >= 2 && (!e->graph_ok || e->graph_dt != dt || run > e->graph_steps)) {
                 r = capture_steps(e, dt, run);
                 if (r) return r;
             }
