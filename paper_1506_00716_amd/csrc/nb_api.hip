@@ -1794,6 +1794,7 @@ nb_status nb_compute_forces_noalloc(nb_ctx* ctx, const nb_params* p, const doubl
     for (int attempt = 0; attempt < 4; ++attempt) {
         // place() clears the counters and flags a build reads; the per-atom data
         // go straight from the caller's arrays into the array's particle slots
+        // (has_particles stays false: there are no host copies for place() to upload)
         r = place(&s, up, false, false, x_dev, f_dev);
         if (r) return r;
         hipStream_t st = ctx->stream;
@@ -1802,7 +1803,6 @@ nb_status nb_compute_forces_noalloc(nb_ctx* ctx, const nb_params* p, const doubl
             HIPCHK(ctx, hipMemcpyAsync((void*)s.h.sig, sigma, sizeof(double) * N, hipMemcpyHostToDevice, st));
             HIPCHK(ctx, hipMemcpyAsync((void*)s.h.eps, epsilon, sizeof(double) * N, hipMemcpyHostToDevice, st));
         }
-        s.has_particles = true;
         r = do_build(&s);
         if (r == NB_ERR_CAPACITY && s.needed_bytes <= kNoallocBytes) continue;
         if (r) return r;
