@@ -556,9 +556,15 @@ __global__ __launch_bounds__(256, WAVES) void k_force8(const SysDev* __restrict_
 //  - an i-cluster's forces are summed over the entries in order, so after a barrier
 //    wave w sums those of i-clusters 2w and 2w + 1 from the factors (6 instructions
 //    for a cluster pair).
-// An item of weight <= kSplitWeight has at most 31 entries and 97 cluster pairs (an
-// item reaches up to an entry's weight before its cut; the weights of entry_weight).
+// An item reaches from the entry that holds its cut to the one that holds the next, so
+// beyond its first entry it weighs less than kSplitWeight: that bounds its entries (by
+// the least weight of one) and its cluster pairs (an entry of all kGroup i-clusters has
+// the most for its weight).
 constexpr int kSplitWeight = 256, kSplitEnt = 32, kSplitPairs = 97 + kGroup - 1;
+static_assert(1 + (kSplitWeight - 1) / (kEntW0 + kEntW1) <= kSplitEnt, "an item's entries exceed their LDS");
+static_assert(kGroup + (kSplitWeight - 1) * kGroup / kEntWMax <= kSplitPairs - (kGroup - 1),
+              "an item's cluster pairs exceed their LDS (an entry may write kGroup factors from its first)");
+static_assert(kSplitEnt == 32, "the scan over the entries covers 32 lanes");
 template <int COUL, int LJ>
 __global__ __launch_bounds__(256, 4) void k_force8_split(const SysDev* __restrict__ table, int n_sys,
                                                          const int* __restrict__ item_prefix, int red_row,
