@@ -136,9 +136,11 @@ nb_status pme_fork(nb_sys* s, const double* x, bool ener);
 nb_status pme_join(nb_sys* s);
 int few_items(const nb_sys* s);  // launch_force's, of one system
 nb_status pair_beside_pme(nb_sys* s, const double* x, bool ener, bool prune, int guard = -1);
-// the pair kernel's grid beside the PME kernels: 4 blocks of 4 waves per CU.  At 100
-// registers they leave a SIMD 96 more, a slot for the PME kernels' waves (24,389 atoms
-// on 52^3 points 74.2 us a step in dynamics; 75.5 with 3 blocks, 76.7 with 2)
+// the pair kernel's grid beside the PME kernels, for all of its variants: 4 blocks of 4
+// waves per CU.  As measured (us a step in dynamics, 4 blocks and 3): 64,000 atoms 135
+// and 139, with per-atom LJ 139 and 142, energies at every step 169 and 173, pruning 140
+// and 147; 24,389 atoms 73.0 and 73.0, 77.4 and 75.8, 98.0 and 94.9, 76.5 and 76.0; the
+// same up to 8,000 atoms, whose launches have fewer blocks
 int pair_grid_beside_pme(const nb_ctx* c);
 // dynamic-prune guard (no-op without pruning): check = the prune interval that
 // ends here is measured; either way x_prune = x
