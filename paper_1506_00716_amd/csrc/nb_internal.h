@@ -430,8 +430,6 @@ hipError_t launch_page_out(const int* from, int* pinned, int words, hipStream_t 
 hipError_t launch_energy_reduce(const SysDev* table, int n_sys, int trace_row, bool with_ke,
                                 double step_value, hipStream_t s);
 hipError_t launch_kick_drift(const SysDev* table, int n_sys, const Bounds& b, double dt, hipStream_t s);
-hipError_t launch_kick(const SysDev* table, int n_sys, const Bounds& b, double dt, bool ke,
-                       hipStream_t s);
 hipError_t launch_item_prefix(const SysDev* table, int n_sys, int* item_prefix, hipStream_t s,
                               const int* flags = nullptr);
 // fused plain-step kernels: kick + drift + staging; gather + kick (+ kinetic energy)
@@ -443,10 +441,6 @@ hipError_t launch_kick_drift_stage(const SysDev* table, int n_sys, const Bounds&
 // held: nothing moves and no force is stored if the list ran out of capacity
 hipError_t launch_gather_kick(const SysDev* table, int n_sys, const Bounds& b, double dt, bool ke, hipStream_t s,
                               int next = 0, bool open = false, bool held = false);
-hipError_t launch_export_count(const SysDev* table, const Bounds& b, hipStream_t s);
-hipError_t launch_export_write(const SysDev* table, const Bounds& b, int* pairs_dev,
-                               long long cap, hipStream_t s);
-hipError_t launch_stats(const SysDev* table, const Bounds& b, hipStream_t s);
 // relaxation of one system: the force gather with the largest |F|^2 per block
 // (kKeBlocks partials at most), and the move with its staging (see the kernel)
 hipError_t launch_gather_fmax(const SysDev* table, const Bounds& b, hipStream_t s);

@@ -75,39 +75,6 @@ __global__ __launch_bounds__(256) void k_kick_drift(const SysDev* __restrict__ t
     }
 }
 
-// v += dt/2 F/m ; per-block kinetic-energy partial sums (fixed decomposition)
-__global__ __launch_bounds__(256) void k_kick(const SysDev* __restrict__ table, double dt, int ke)
-{
-    const SysDev& d = table[blockIdx.y];
-    __shared__ double sh[256];
-    const int nb = sys_blocks(d.n_atoms);
-    if ((int)blockIdx.x >= nb) {
-        if (ke && threadIdx.x == 0) d.ke_part[blockIdx.x] = 0.0;
-        return;
-    }
-    const int stride = nb * blockDim.x;
-    double acc = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d.n_atoms; i += stride) {
-        const double m = d.mass[i];
-        const double h = 0.5 * dt / m;
-        double s = 0.0;
-        for (int k = 0; k < 3; ++k) {
-            const double v = fma(h, (double)d.f[3 * i + k], d.v[3 * i + k]);
-            d.v[3 * i + k] = v;
-            s += v * v;
-        }
-        acc += 0.5 * m * s;
-    }
-    if (!ke) return;
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) d.ke_part[blockIdx.x] = sh[0];
-}
-
 // List-buffer guard (Verlet displacement criterion): at each rebuild, the
 // largest displacement since the previous build; a pair can only have entered
 // r_cut unlisted if two atoms moved by >= (r_list - r_cut)/2 each.
@@ -220,7 +187,7 @@ __global__ __launch_bounds__(256) void k_state_copy(const SysDev* __restrict__ t
 
 // ---- fused per-slot step kernels (plain steps without a list rebuild) --------
 // Every real atom owns exactly one slot, so per-atom updates can run in cluster
-// order and the FP64 arithmetic is the same as in k_kick_drift / k_kick.
+// order and the FP64 arithmetic is the same as in k_kick_drift.
 
 // v += dt/2 F/m ; x += dt v ; stage the new x into the group-local FP32 SoA
 __global__ __launch_bounds__(256) void k_kick_drift_stage(const SysDev* __restrict__ table, double dt)
@@ -659,16 +626,6 @@ hipError_t launch_energy_reduce(const SysDev* table, int n_sys, int trace_row, b
 hipError_t launch_kick_drift(const SysDev* table, int n_sys, const Bounds& b, double dt, hipStream_t s)
 {
     hipLaunchKernelGGL(k_kick_drift, dim3(atom_blocks(b.max_atoms), n_sys), dim3(256), 0, s, table, dt);
-    return hipGetLastError();
-}
-
-hipError_t launch_kick(const SysDev* table, int n_sys, const Bounds& b, double dt, bool ke,
-                       hipStream_t s)
-{
-    // blocks beyond a member's own count write zero partials and exit; partials
-    // past the grid stay zero from system creation
-    hipLaunchKernelGGL(k_kick, dim3(atom_blocks(b.max_atoms), n_sys), dim3(256), 0, s, table, dt,
-                       ke ? 1 : 0);
     return hipGetLastError();
 }
 
