@@ -342,9 +342,8 @@ __global__ __launch_bounds__(256) void k_gather(const SysDev* __restrict__ table
     // partial rows written by the force kernel: a list whose build ran out of
     // capacity has none (its offsets may point past the partial arrays, so the
     // row ranges below are clamped to what exists)
-    const int n_it = gld(n_items_p), ent_w = gld(n_ent_p);
-    const bool over = ent_w < 0;
-    const int n_en = over ? ~ent_w : ent_w;
+    const int n_it = gld(n_items_p), ent_w = __builtin_amdgcn_readfirstlane(gld(n_ent_p));
+    const int n_en = ent_w ^ (ent_w >> 31);  // (~ of it marks a capacity exceeded)
     const int n_cl = __builtin_amdgcn_readfirstlane(gld(n_groups_p)) * kGroup;
     const int nb = cluster_blocks(n_cl);           // kinetic-energy partials
     const int stride = nb * 4 * M;                 // slots per pass of all waves
@@ -359,14 +358,13 @@ __global__ __launch_bounds__(256) void k_gather(const SysDev* __restrict__ table
         if (FMAX && threadIdx.x == 0) gst(&d.fmax_part[bx], 0.0);
         return;
     }
-    if (KICK && over && held) return;
     bool bad = false;
     double kin = 0.0;
     // the largest squared displacement since the last build (NEXT 1) or squared
     // force (FMAX)
     double disp_m = 0.0;
     // (a wave of the last block may have no partial of its own)
-    const int end = !WIDE || part < nb ? n_cl * M : 0;
+    const int end = (!WIDE || part < nb) && !(KICK && held && ent_w < 0) ? n_cl * M : 0;
     for (int base = w0; base < end; base += stride) {
         // No branch or conditional load sits between the loads of a round trip, so
         // none waits on another.  Empty clusters (no partials are written for
