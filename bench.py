@@ -48,8 +48,8 @@ FLOPS_PER_PAIR = {"ewald": 36, "rf": 30, "none": 26}
 TIMING_STRIDE = 7
 
 FORCE_TRAFFIC = {
-    "786f8f5986e925bc785c6b17270cd6ef96680f4a4041a4e3c9f2e73a0cd65c63":
-        {"fetch_bytes": 2 * 1438.3 * 1024, "write_bytes": 8439.7 * 1024},
+    "a774606b1e2120d16bf9d7d7b238892af0e27a61eb3bb27ad46a10ab262fd942":
+        {"fetch_bytes": 2 * 1411.3 * 1024, "write_bytes": 8508.9 * 1024},
 }
 
 
@@ -57,7 +57,7 @@ FORCE_TRAFFIC = {
 # kernels of the calibrated FETCH_SIZE + WRITE_SIZE), keyed by the SHA-256 of
 # the list builder's source; null for other sources.
 BUILD_TRAFFIC = {
-    "6d51a392c46240d24b512fdfd692eb28c711732e75759a82f68ea9a44c057499": 14.754e6,
+    "fdde660b27ac90f6063f3ec0434fde7038fc55b8963032d553d97de82bd234a9": 14.654e6,
 }
 
 
@@ -74,9 +74,10 @@ def _src_hash(names):
 # VALU counter FLOP per launch of the same kernel on the default workload:
 # 64 x (ADD_F32 + MUL_F32 + TRANS_F32) + 128 x FMA_F32 wave instructions from
 # one rocprofv3 --pmc pass (every lane of every issued instruction, masked-off
-# pairs included), keyed like FORCE_TRAFFIC.
+# pairs included; without the FMAs of zero with a coordinate that start the sums, 3
+# an entry and 24 an item, 0.272 M), keyed like FORCE_TRAFFIC.
 FORCE_VALU_FLOP = {
-    "786f8f5986e925bc785c6b17270cd6ef96680f4a4041a4e3c9f2e73a0cd65c63": 588.6e6,
+    "a774606b1e2120d16bf9d7d7b238892af0e27a61eb3bb27ad46a10ab262fd942": 591.0e6,
 }
 
 
